@@ -403,7 +403,7 @@ size_t gq_lnq_codebook_workspace_bytes(int64_t d_out, int64_t d_in, int32_t G, i
  *   codebook[j,:] = (P^T H[k] P + lam I)^-1 P^T H[k] W[j,:],   P[i,q] = 1 if Q[j,i] == q else 0,
  *
  * the minimiser of (W[j,:] - P c)^T H[k] (W[j,:] - P c) + lam |c|^2 over c.  P^T H[k] is
- * accumulated in fp32 from exact products (H enters as three bf16 terms), the n_levels x
+ * accumulated exactly from H in 30-bit fixed point per row (integer matrix cores) and rounded to fp32, the n_levels x
  * n_levels system is solved in fp64 by Gaussian elimination with partial pivoting.  A grid
  * point no coordinate is assigned to gets the value 0 (lam > 0).
  *

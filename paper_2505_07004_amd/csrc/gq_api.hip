@@ -245,7 +245,7 @@ int gq_lnq_codebook(const float* W, int64_t d_out, int64_t d_in, int64_t ld_w, c
                                           (hipStream_t)hip_stream));
 }
 
-// gq_lnq keeps the two steps' preparations of H (split coefficients of the CD step, the three bf16 terms of
+// gq_lnq keeps the two steps' preparations of H (split coefficients of the CD step, the four digits of
 // the codebook step) side by side, so that only the first round of the alternation builds them.
 static size_t lnq_cd_part(int64_t d_out, int64_t d_in, int32_t G) {
   return (gq_cd_workspace_bytes(d_out, d_in, G) + 255) / 256 * 256;
