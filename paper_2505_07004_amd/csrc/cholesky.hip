@@ -8,8 +8,7 @@
 // Both are one algorithm on a working matrix A' = U^T U, U upper triangular, processed by block rows
 // of 128 in fp32:  A' = A gives L = U^T;  A'[a][b] = A[d-1-a][d-1-b] gives R[i][j] = U[d-1-j][d-1-i].
 // Per block row:  (1) the 128 x 128 diagonal block is factored and (2) the panel to its right is solved
-// against it, U12 = U11^-T A12, in one launch (both with the block in registers, 8 x 8 per thread, eight
-// rows at a time published through LDS);
+// against it, U12 = U11^-T A12, in one launch (both in LDS, 32 rows at a time);
 // (3) the trailing upper triangle is updated, A22 -= U12^T U12, on the bf16 matrix cores at fp32
 // accuracy (U12 as three bf16 terms, six products).
 // Only the upper triangle of H is read.  A non-positive pivot is recorded in info[k] (its
@@ -96,204 +95,261 @@ __device__ __forceinline__ int64_t p3_index(int64_t k, int term, int64_t row, in
 __device__ __forceinline__ float lane_value(float v, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
-// between an LDS write by one lane and the read of it by another lane of the same wave
-__device__ __forceinline__ void wave_lds_fence() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_wave_barrier();
-}
 
 // (1) + (2) One block row: the diagonal block A11 = U11^T U11 at (r0, r0) and the panel to its right,
-// U12 = U11^-T A12, in one launch.  A workgroup owns 128 columns of the panel; its threads 256..511 hold
-// that 128 x 128 tile of A12 in registers (thread (tr, tc) of 16 x 16 the 8 x 8 tile at rows 8 tr, columns
-// 8 tc), its threads 0..255 hold the diagonal block the same way: every workgroup factors the diagonal
-// block again beside its panel (the two halves run on different waves, so this costs no time and saves
-// the launch and the round trip of U11 through memory that a separate kernel needs).  Eight rows at a time:
-//   a. the thread of the diagonal 8 x 8 tile factors it on its own (eight pivots, no barrier) and
-//      publishes the 8 x 8 factor;
-//   b. the other owners of these eight rows, of the diagonal block and of the panel alike, solve their
-//      tiles against it (forward substitution, eight steps, no barrier) and publish the finished rows;
-//   c. every tile further down subtracts the product of its eight row entries (from the diagonal
-//      block's rows) and its eight column entries: a rank-8 update.
-// Two barriers per eight rows (the published data alternate between two buffers).  Launched with 256
-// threads there is no panel (the last block row).  Workgroup 0 stores U11 and reports bad pivots; U11
+// U12 = U11^-T A12, in one launch.  A workgroup owns 128 columns of the panel and factors the diagonal block again
+// beside it (which costs less than a launch and the trip of U11 through memory).  Both lie side by side in LDS,
+// S[128 rows][256 columns], and are worked through 32 rows at a time:
+//   a. factor   one wave, a column per lane (its 32 entries in registers): the 32 x 32 diagonal block; per pivot one
+//               square root, one reciprocal, and the pivot row's entries read from its lanes (v_readlane).
+//   b. solve    four waves, a column per lane: the rest of the 32 rows by forward substitution against the factor
+//               in LDS (broadcast reads).
+//   c. update   everything below, 32 x 32 tiles, minus the product of the 32 finished rows with themselves on the fp32
+//               matrix cores.  The first wave updates the next diagonal tile and goes straight on to factor it, the
+//               other seven take the rest: only that tile, a and b are on the chain.
+// Two barriers per 32 rows.  What bounds it is the chain of pivots (32 x 0.12 us per factorization; 2.7 us a substitution).  (Before:
+// eight rows at a time, all tiles in registers, two barriers per eight rows and a rank-8 update on the vector units:
+// 64 us per block row at d = 4096, now 45.)  Every entry sees the same fused multiply-adds in
+// the same order as then (the fp32 matrix instruction chains them row by row): the factor is the same to the last bit.
+// Launched with panel = 0 there is no panel (the last block row).  Workgroup 0 stores U11 and reports bad pivots; U11
 // goes to a buffer of its own (Ud[k][block][128][128]), not over A11, which workgroups that start
 // later still have to read.
 // Rows and columns past the end of the matrix are those of the identity.
+constexpr int kSub = 32;                              // rows of a pass
+// floats per row of S: rows four apart lie 32 banks apart, so that the two half-waves of the tile accesses below (four
+// rows apart) use different banks
+constexpr int kSPitch = 2 * kNb + 8;
+
+// a: the diagonal block at row and column 32 b of S (one wave; the upper half-wave repeats the lower).  Returns the
+// block's bad pivots as a bit mask.
+// The next pivot is brought up to date first, and its square root and reciprocal are worked out between the rest of
+// the current pivot's updates, which are issued in groups (multipliers read from their lanes, then the products) so
+// that no instruction waits for the one before; the scheduling barriers keep that order.
+__device__ __noinline__ unsigned chol_factor32(float* S, float* rdiag, int b, int lane) {
+  const int lc = lane % kSub;
+  const int base = kSub * b * kSPitch + kSub * b + lc;
+  float v[kSub], rd = 0.f, pv = 1.f;                          // pv: this lane's own pivot
+#pragma unroll
+  for (int i = 0; i < kSub; ++i) v[i] = S[base + i * kSPitch];
+  float p = lane_value(v[0], 0), sp = 1.f, isp = 1.f, nsp = 1.f, nisp = 1.f;
+  auto chain = [&](int j, int step) {                         // pivot j, one step of it
+    if (step == 0) {
+      pv = lc == j ? p : pv;
+      p = p > 0.f ? p : 1.f;
+      nsp = __builtin_amdgcn_sqrtf(p);
+    } else if (step == 1) {
+      nisp = __builtin_amdgcn_rcpf(nsp);
+    }
+  };
+  chain(0, 0);
+  chain(0, 1);
+#pragma unroll
+  for (int j = 0; j < kSub; ++j) {
+    sp = nsp;
+    isp = nisp;
+    const float u = lc == j ? sp : v[j] * isp;                // row j of the factor, this lane's column
+    rd = lc == j ? isp : rd;
+    v[j] = u;
+    if (j + 1 == kSub) break;
+    v[j + 1] -= lane_value(u, j + 1) * u;
+    p = lane_value(v[j + 1], j + 1);
+    constexpr int kGroup = 6;
+#pragma unroll
+    for (int g = 0; g < 5; ++g) {
+      float m[kGroup];
+#pragma unroll
+      for (int e = 0; e < kGroup; ++e) {
+        const int i = j + 2 + kGroup * g + e;
+        if (i < kSub) m[e] = lane_value(u, i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (g < 2) chain(j + 1, g);
+#pragma unroll
+      for (int e = 0; e < kGroup; ++e) {
+        const int i = j + 2 + kGroup * g + e;
+        if (i < kSub) v[i] -= m[e] * u;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (lane < kSub) {
+    rdiag[lane] = rd;
+#pragma unroll
+    for (int i = 0; i < kSub; ++i) S[base + i * kSPitch] = lane >= i ? v[i] : 0.f;
+  }
+  return (unsigned)__ballot(!(pv > 0.f));                     // (a NaN is bad as well; the halves agree)
+}
+
+// b: the rest of the rows 32 b .. + 31, column c per lane, by forward substitution; the factor's rows are read from LDS
+// 16 bytes at a time, the same ones by all lanes.
+__device__ __noinline__ void chol_solve32(float* S, const float* rdiag, int b, int c) {
+  const float* const U = &S[kSub * b * kSPitch + kSub * b];
+  float v[kSub];
+#pragma unroll
+  for (int i = 0; i < kSub; ++i) v[i] = S[(kSub * b + i) * kSPitch + c];
+#pragma unroll
+  for (int j = 0; j < kSub; ++j) {
+    const float x = v[j] * rdiag[j];
+    v[j] = x;
+#pragma unroll
+    for (int q = 0; q < kSub / 4; ++q) {
+      if (4 * q + 3 <= j) continue;
+      const f32x4 u = *reinterpret_cast<const f32x4*>(U + j * kSPitch + 4 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * q + e > j) v[4 * q + e] -= u[e] * x;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kSub; ++i) S[(kSub * b + i) * kSPitch + c] = v[i];
+}
+
 __global__ __launch_bounds__(512) void chol_block_row_kernel(float* __restrict__ Uw, int64_t d, int64_t r0,
                                                              float* __restrict__ Ud, unsigned short* __restrict__ P3,
-                                                             int64_t ldc, int koff, int* __restrict__ info) {
-  __shared__ __attribute__((aligned(16))) float dtile[2][8][8];
-  __shared__ __attribute__((aligned(16))) float draw[8][8];            // the diagonal tile of a pass before it is factored
-  __shared__ __attribute__((aligned(16))) float rows[2][8][2 * kNb];   // columns 0..127: diagonal block, 128..255: panel
-  __shared__ int bad;
+                                                             int64_t ldc, int koff, int panel, int* __restrict__ info) {
+  __shared__ __attribute__((aligned(16))) float S[kNb * kSPitch];
+  __shared__ float rdiag[kSub];                               // reciprocals of the diagonal of the pass's factor
   const int k = blockIdx.y;
   float* Uk = Uw + (int64_t)k * d * d;
-  const int tid = threadIdx.x, role = tid / 256, tr = (tid % 256) / 16, tc = tid % 16;
-  const int cb = role * kNb + 8 * tc;                                    // this thread's columns in `rows`
-  const int64_t c0 = role == 0 ? r0 : r0 + kNb + (int64_t)blockIdx.x * kNb;   // first global column of this half's tile
-  if (tid == 0) bad = -1;
-  // The thread's 8 x 8 tile: 32 bytes per row, as two 16-byte loads where the rows are 16-byte aligned
-  // (d a multiple of 4) and the eight columns lie inside the matrix; all loads in flight at once.
-  const bool vec_rows = d % 4 == 0;                          // uniform
-  float a[8][8];
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int64_t p0 = r0 + kNb + (int64_t)blockIdx.x * kNb;    // first global column of the panel part
+
+  // Load: 16 bytes per lane where the rows are 16-byte aligned (d a multiple of 4), all loads of a thread in flight.
+  // Thread -> columns 4 (tid % 64) .. + 3 of the 256, rows tid / 64, + 8, ...
   {
-    const int64_t gc0 = c0 + 8 * tc;
-    const bool whole = vec_rows && gc0 + 7 < d;
-    f32x4 in4[8][2];
+    const int c4 = 4 * lane, half = c4 / kNb;                  // half 0: diagonal block, 1: panel
+    const int64_t gc = (half == 0 ? r0 : p0) + c4 % kNb;
+    f32x4 in4[16];
+    if (d % 4 == 0) {                                          // uniform; four columns are then inside or outside together
+      const int64_t gcc = gc < d ? gc : d - 4;                 // addresses clamped into the matrix, no branch around a load
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int64_t gr = r0 + 8 * tr + i;
-      if (whole && gr < d) {
-        in4[i][0] = *reinterpret_cast<const f32x4*>(Uk + gr * d + gc0);
-        in4[i][1] = *reinterpret_cast<const f32x4*>(Uk + gr * d + gc0 + 4);
-      } else {
+      for (int i = 0; i < 16; ++i) {
+        const int64_t gr = r0 + wave + 8 * i;
+        in4[i] = *reinterpret_cast<const f32x4*>(Uk + (gr < d ? gr : d - 1) * d + gcc);
+      }
+    } else {
 #pragma unroll
-        for (int l = 0; l < 8; ++l) in4[i][l / 4][l % 4] = (gr < d && gc0 + l < d) ? Uk[gr * d + gc0 + l] : 0.f;
+      for (int i = 0; i < 16; ++i) {
+        const int64_t gr = r0 + wave + 8 * i;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) in4[i][l] = Uk[(gr < d ? gr : d - 1) * d + (gc + l < d ? gc + l : d - 1)];
       }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 16; ++i) {
+      const int r = wave + 8 * i;
 #pragma unroll
-      for (int l = 0; l < 8; ++l) {
-        const int r = 8 * tr + i, c = 8 * tc + l;
-        const bool in = r0 + r < d && gc0 + l < d && (role == 1 || r <= c);
-        a[i][l] = in ? in4[i][l / 4][l % 4] : ((role == 0 && r == c) ? 1.f : 0.f);
+      for (int l = 0; l < 4; ++l) {
+        // below the diagonal of the diagonal block the matrix holds nothing; past its end, the identity
+        const bool in = r0 + r < d && gc + l < d && (half == 1 || r <= c4 + l);
+        in4[i][l] = in ? in4[i][l] : ((half == 0 && r == c4 + l) ? 1.f : 0.f);
       }
+      *reinterpret_cast<f32x4*>(&S[r * kSPitch + c4]) = in4[i];
+    }
   }
   __syncthreads();
-  for (int jb = 0; jb < 16; ++jb) {
-    const int buf = jb & 1;
-    if (role == 0 && tr / 4 == jb / 4) {                      // a. the diagonal tile (uniform: the wave that holds it)
-      // Its owner hands the tile to eight lanes of its wave (those of tile row jb, columns 0..7 of it), one
-      // column each; the eight pivots then cost one cross-lane read each instead of a chain through all
-      // 36 elements in one lane.  Same operations on the same values as the factorization of an 8 x 8 tile
-      // by one thread.  LDS accesses of one wave execute in order; the fence only stops the compiler.
-      if (tr == jb && tc == jb) {
+
+  int bad = -1;                                               // first bad pivot of the block (wave 0)
+  auto update = [&](int b, int bi, int ct) {                  // tile (rows 32 bi, columns 32 ct) -= X^T X of the rows 32 b
+    const int h = lane / 32, lc = lane % 32;
+    float* const T = &S[(kSub * bi + 4 * h) * kSPitch + kSub * ct + lc];
+    const float* const X = &S[(kSub * b + h) * kSPitch + lc];
+    f32x16 acc;
+    float fa[16], fb[16];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          *reinterpret_cast<f32x4*>(&draw[i][0]) = f32x4{a[i][0], a[i][1], a[i][2], a[i][3]};
-          *reinterpret_cast<f32x4*>(&draw[i][4]) = f32x4{a[i][4], a[i][5], a[i][6], a[i][7]};
-        }
-      }
-      wave_lds_fence();
-      const int hl = tc & 7;
-      float col[8];
+    for (int t = 0; t < 16; ++t) {
+      fa[t] = -X[2 * t * kSPitch + kSub * bi];                // rows 2 t and, in the upper half-wave, 2 t + 1, in order
+      fb[t] = X[2 * t * kSPitch + kSub * ct];
+      acc[t] = T[(8 * (t / 4) + t % 4) * kSPitch];            // register r of lane l: row 8*(r/4)+4*(l/32)+(r%4), column l%32
+    }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) col[i] = draw[i][hl];
-      const int lane_base = 16 * (jb % 4);                    // lane of (tile row jb, tile column 0) in this wave
+    for (int t = 0; t < 16; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[t], fb[t], acc, 0, 0, 0);
 #pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        float p = lane_value(col[jj], lane_base + jj);
-        const bool ok = p > 0.f;                              // false for NaN as well (uniform)
-        if (!ok && tr == jb && tc == 0 && bad < 0) bad = 8 * jb + jj;
-        p = ok ? p : 1.f;
-        const float sp = __builtin_amdgcn_sqrtf(p), isp = __builtin_amdgcn_rcpf(sp);
-        const float u = hl == jj ? sp : col[jj] * isp;        // row jj of the factor, this lane's column
-        col[jj] = u;
-#pragma unroll
-        for (int i = jj + 1; i < 8; ++i) col[i] -= lane_value(u, lane_base + i) * u;
-      }
-      if (tr == jb && tc < 8) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float v = hl >= i ? col[i] : 0.f;
-          dtile[buf][i][hl] = v;
-          rows[buf][i][8 * jb + hl] = v;
-        }
-      }
-      wave_lds_fence();
-      if (tr == jb && tc == jb) {                             // the owner takes the factored tile back
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const f32x4 lo = *reinterpret_cast<const f32x4*>(&dtile[buf][i][0]);
-          const f32x4 hi = *reinterpret_cast<const f32x4*>(&dtile[buf][i][4]);
-#pragma unroll
-          for (int l = 0; l < 4; ++l) {
-            a[i][l] = lo[l];
-            a[i][4 + l] = hi[l];
-          }
-        }
-      }
+    for (int t = 0; t < 16; ++t) T[(8 * (t / 4) + t % 4) * kSPitch] = acc[t];
+  };
+
+  auto factor = [&](int b) {
+    const unsigned mask = chol_factor32(S, rdiag, b, lane);
+    if (mask && bad < 0) bad = kSub * b + __builtin_ctz(mask);
+  };
+  if (wave == 0) factor(0);
+  for (int b = 0; b < kNb / kSub; ++b) {
+    __syncthreads();                                          // the factor of pass b is in LDS, and all of pass b - 1's update
+    if (wave <= 3) {
+      const int c = kSub * (b + 1) + 64 * wave + lane;        // columns 32 (b + 1) .. 255
+      if (c < 2 * kNb) chol_solve32(S, rdiag, b, c);
     }
     __syncthreads();
-    if (tr == jb && (role == 1 || tc > jb)) {                 // b. the rest of the eight rows: U_dd^T X = A
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        const float rp = __builtin_amdgcn_rcpf(dtile[buf][jj][jj]);
-#pragma unroll
-        for (int l = 0; l < 8; ++l) {
-          float v = a[jj][l];
-#pragma unroll
-          for (int i = 0; i < jj; ++i) v -= dtile[buf][i][jj] * a[i][l];
-          a[jj][l] = v * rp;
+    if (b + 1 == kNb / kSub) break;
+    if (wave == 0) {
+      update(b, b + 1, b + 1);
+      factor(b + 1);
+    } else {
+      // the other tiles, row by row: rows 32 bi, column tiles bi .. 7 (the first row from b + 2 on)
+      int t = wave - 1, bi = b + 1, ct0 = b + 2;
+      while (bi < kNb / kSub) {
+        const int n = 2 * kNb / kSub - ct0;                   // tiles of this row of tiles
+        if (t >= n) {
+          t -= n;
+          ++bi;
+          ct0 = bi;
+        } else {
+          update(b, bi, ct0 + t);
+          t += 7;
         }
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        *reinterpret_cast<f32x4*>(&rows[buf][i][cb]) = f32x4{a[i][0], a[i][1], a[i][2], a[i][3]};
-        *reinterpret_cast<f32x4*>(&rows[buf][i][cb + 4]) = f32x4{a[i][4], a[i][5], a[i][6], a[i][7]};
-      }
-    }
-    __syncthreads();
-    if (tr > jb && (role == 1 || tc >= tr)) {                 // c. rank-8 update of everything further down
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) {
-        float f[8], cl[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) f[i] = rows[buf][jj][8 * tr + i];
-#pragma unroll
-        for (int l = 0; l < 8; ++l) cl[l] = rows[buf][jj][cb + l];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int l = 0; l < 8; ++l) a[i][l] -= f[i] * cl[l];
       }
     }
   }
-  if (role == 1) {
-    const int64_t gc0 = c0 + 8 * tc;
-    const bool whole = vec_rows && gc0 + 7 < d;
+
+  if (panel) {
+    const int c4 = 4 * (tid % 32);
+    const int64_t gc = p0 + c4;
+    const bool whole = d % 4 == 0 && gc + 3 < d;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int64_t gr = r0 + 8 * tr + i;
-      if (whole && gr < d) {
-        *reinterpret_cast<f32x4*>(Uk + gr * d + gc0) = f32x4{a[i][0], a[i][1], a[i][2], a[i][3]};
-        *reinterpret_cast<f32x4*>(Uk + gr * d + gc0 + 4) = f32x4{a[i][4], a[i][5], a[i][6], a[i][7]};
-      } else {
+    for (int i = 0; i < 8; ++i) {                             // rows tid / 32, + 16, ...
+      const int r = tid / 32 + 16 * i;
+      const int64_t gr = r0 + r;
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&S[r * kSPitch + kNb + c4]);
+      if (gr < d) {
+        if (whole) {
+          *reinterpret_cast<f32x4*>(Uk + gr * d + gc) = v;
+        } else {
 #pragma unroll
-        for (int l = 0; l < 8; ++l)
-          if (gr < d && gc0 + l < d) Uk[gr * d + gc0 + l] = a[i][l];
+          for (int l = 0; l < 4; ++l)
+            if (gc + l < d) Uk[gr * d + gc + l] = v[l];
+        }
       }
     }
     // ... and once more for the trailing update: three bf16 terms in the order the update consumes them
-    // (p3_index): a thread's eight rows of one column are 16 bytes per term
+    // (p3_index): eight rows of one column are 16 bytes per term
 #pragma unroll
-    for (int l = 0; l < 8; ++l) {
+    for (int i = 0; i < 4; ++i) {
+      const int c = tid % kNb, r8 = 8 * (tid / kNb + 4 * i);
       unsigned short t[3][8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) split3_bf16(a[i][l], t[0][i], t[1][i], t[2][i]);
-      const int64_t gc = c0 + 8 * tc + l;                         // < ldc: the buffer covers whole panels
+      for (int e = 0; e < 8; ++e) split3_bf16(S[(r8 + e) * kSPitch + kNb + c], t[0][e], t[1][e], t[2][e]);
 #pragma unroll
       for (int term = 0; term < 3; ++term) {
         u32x4 w;
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = (unsigned)t[term][2 * e] | ((unsigned)t[term][2 * e + 1] << 16);
-        *reinterpret_cast<u32x4*>(P3 + p3_index(k, term, koff + 8 * tr, gc, ldc)) = w;
+        *reinterpret_cast<u32x4*>(P3 + p3_index(k, term, koff + r8, p0 + c, ldc)) = w;   // column < ldc: whole panels
       }
     }
-  } else if (blockIdx.x == 0) {
+  }
+  if (blockIdx.x == 0) {
     float* Ub = Ud + ((int64_t)k * ((d + kNb - 1) / kNb) + r0 / kNb) * (kNb * kNb);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      f32x4 o[2];
+      const int r = tid / 32 + 16 * i, c4 = 4 * (tid % 32);
+      f32x4 v = *reinterpret_cast<const f32x4*>(&S[r * kSPitch + c4]);
 #pragma unroll
-      for (int l = 0; l < 8; ++l) o[l / 4][l % 4] = (8 * tr + i <= 8 * tc + l) ? a[i][l] : 0.f;
-      *reinterpret_cast<f32x4*>(Ub + (8 * tr + i) * kNb + 8 * tc) = o[0];
-      *reinterpret_cast<f32x4*>(Ub + (8 * tr + i) * kNb + 8 * tc + 4) = o[1];
+      for (int l = 0; l < 4; ++l) v[l] = r <= c4 + l ? v[l] : 0.f;
+      *reinterpret_cast<f32x4*>(Ub + r * kNb + c4) = v;
     }
+    if (tid == 0 && bad >= 0 && info && info[k] == 0) info[k] = (int)(r0 + bad) + 1;
   }
-  __syncthreads();
-  if (tid == 0 && blockIdx.x == 0 && bad >= 0 && info && info[k] == 0) info[k] = (int)(r0 + bad) + 1;
 }
 
 // (3) Trailing update: for 128 x 128 tiles (ti <= tj) of the upper triangle with origin t0,
@@ -713,8 +769,8 @@ hipError_t launch_damped_cholesky(const float* H, int64_t d, int G, double damp_
   auto block_row = [&](int64_t r0, int koff, unsigned short* P3) -> hipError_t {
     const int64_t trail = d - (r0 + kNb);
     const int64_t tt = trail > 0 ? (trail + kNb - 1) / kNb : 0;
-    chol_block_row_kernel<<<dim3((unsigned)(tt > 0 ? tt : 1), (unsigned)G), dim3(tt > 0 ? 512 : 256), 0, st>>>(
-        Uw, d, r0, Ud, P3, L.ldc, koff, info);
+    chol_block_row_kernel<<<dim3((unsigned)(tt > 0 ? tt : 1), (unsigned)G), dim3(512), 0, st>>>(
+        Uw, d, r0, Ud, P3, L.ldc, koff, tt > 0 ? 1 : 0, info);
     return hipGetLastError();
   };
   int64_t emitted = 0;                                        // rows of U already on their way to F
