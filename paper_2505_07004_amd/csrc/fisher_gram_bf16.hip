@@ -666,8 +666,16 @@ constexpr int kMinUnitsPerWorkgroup = 32;
 
 constexpr int64_t kMinSegmentSteps = 32;   // a segment of an item's token steps is at least 1024 tokens
 constexpr int64_t kMaxSegments = 3;        // more of them cost more in parked tiles than the shared panels save
+// Whole items only (workgroup q computes items q, q + 256, ...; nothing is parked) where the idle workgroups of the last
+// round cost less than cutting the left-over items does.  An item takes about kItemUs plus 1 us per token step; cutting
+// costs about kCutUs (parking the parts, adding them, a launch).
+// Measured (us a call, cut / whole; n, d, G): 112 / 67 (1500, 5000, 1), 75 / 57 (1536, 1500, 3),
+// 57 / 49 (1500, 700, 1), 264 / 180 (6400, 5000, 1), 82 / 29 (300, 3000, 1), 38 / 39 (1000, 1000, 1); the two-term pass over
+// the 160 heaviest tokens of X[10007, 1543], G = 3: 163 -> 25.
+constexpr int64_t kItemUs = 22, kCutUs = 70;
 struct Plan {
   int gpc, n_gsets, segs;
+  bool whole;                                                 // whole items only: nothing is parked
   int64_t n_pad, n_items, P, seg_steps;
   size_t sp_bytes, partial_bytes;
   int64_t n_units() const { return n_items * segs; }
@@ -697,10 +705,16 @@ Plan make_plan(int64_t n, int64_t d_in, int G, bool with_workspace = true) {
       pl.segs = (int)count;
     }
   }
-  if (!with_workspace) P = pl.n_items < kMaxWorkgroups ? pl.n_items : kMaxWorkgroups;   // whole items only
+  const int64_t slots = (pl.n_items + kMaxWorkgroups - 1) / kMaxWorkgroups * kMaxWorkgroups;   // of whole rounds
+  pl.whole = !with_workspace || (slots - pl.n_items) * (kItemUs + steps) <= kCutUs * kMaxWorkgroups;
+  if (pl.whole) {
+    P = pl.n_items < kMaxWorkgroups ? pl.n_items : kMaxWorkgroups;
+    pl.segs = 1;
+    pl.seg_steps = steps;
+  }
   pl.P = P;
   pl.sp_bytes = ((size_t)(pl.n_pad * G) * sizeof(float) + 255) / 256 * 256;
-  pl.partial_bytes = (size_t)((pl.segs > 1 ? 4 : 2) * P) * kTileFloats * sizeof(float);
+  pl.partial_bytes = pl.whole ? 0 : (size_t)((pl.segs > 1 ? 4 : 2) * P) * kTileFloats * sizeof(float);
   return pl;
 }
 
@@ -746,11 +760,11 @@ hipError_t launch_groups(const void* X, int64_t n, int64_t d_in, int64_t ld, con
     return launch_fisher_gram_bf16_wide(X, n, d_in, ld, s, ld_s, G, H, accumulate, ws, no_partials, st);
   const Plan pl = make_plan(n, d_in, G, !no_partials);
   float* sp = (float*)ws;
-  float* partial = no_partials ? nullptr : (float*)((char*)ws + pl.sp_bytes);
+  float* partial = pl.whole ? nullptr : (float*)((char*)ws + pl.sp_bytes);
   pack_weights_kernel<<<dim3((unsigned)((pl.n_pad + 255) / 256)), dim3(256), 0, st>>>(s, ld_s, n, G, pl.n_pad, sp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int64_t left_over = no_partials ? 0 : pl.n_units() % pl.P;
+  const int64_t left_over = pl.whole ? 0 : pl.n_units() % pl.P;
   const int64_t fix_items = pl.segs > 1 ? pl.n_items : left_over;   // segments: every item is summed from its parts
   const dim3 grid((unsigned)pl.P), fix((unsigned)(fix_items > 0 ? fix_items : 1), (unsigned)(kMA * kNB));
   const int segs = pl.segs, seg_steps = (int)pl.seg_steps;
