@@ -120,13 +120,18 @@ __global__ __launch_bounds__(256) void cd_prep_kernel(const float* __restrict__ 
 // triangular factor R of the damped matrix, A = R R^T: the feedback a coordinate i receives from an
 // EARLIER coordinate i' is R[i'][i] / R[i][i] per unit of error, later coordinates give none:
 //   Ht[i][i'] = R[i'][i] / R[i][i]  for i' < i,  0 otherwise.
+// Only blocks of 128 on and below the diagonal are written: the pass reads no other (a block's targets take what lies
+// before it).  Bound by memory; W[4096,4096], G = 4: 97 us with the zeros above, 62 us without.
 __global__ __launch_bounds__(256) void ldlq_prep_kernel(const float* __restrict__ R, int64_t d, int64_t ldp,
                                                         unsigned short* __restrict__ Hth,
                                                         unsigned short* __restrict__ Htl, float* __restrict__ Cd) {
   __shared__ float tile[64][65];
   __shared__ float diag[64];
   const int k = blockIdx.z;
-  const int ti = blockIdx.y, tj = blockIdx.x;              // tile of rows i, of columns i'
+  int ti, tj;                                               // tile of rows i, of columns i': four to a block of 128
+  tri_decode(blockIdx.x / 4, tj, ti);
+  ti = 2 * ti + (int)(blockIdx.x % 4) / 2;
+  tj = 2 * tj + (int)(blockIdx.x % 2);
   const float* Rk = R + (int64_t)k * d * d;
   const int tx = threadIdx.x % 64, ty = threadIdx.x / 64;
   float in[16];                                            // R[i'][i]: rows from the tile of i', columns from the tile of i;
@@ -162,19 +167,6 @@ __global__ __launch_bounds__(256) void ldlq_prep_kernel(const float* __restrict_
 // 16 KiB run of memory instead of 256 pieces of 64 bytes a whole matrix row apart.  Dl = Dh + 32.
 __device__ __forceinline__ int64_t delta_index(int64_t j, int64_t a, int64_t d_out) {
   return ((a >> 5) * d_out + j) * 64 + (a & 31);
-}
-
-// Sequential rounding starts from the weights themselves: What = W, no error yet.
-__global__ __launch_bounds__(256) void ldlq_init_kernel(const float* __restrict__ W, float* __restrict__ What,
-                                                        int64_t d, int64_t ld, int64_t ldp,
-                                                        unsigned short* __restrict__ Dh,
-                                                        unsigned short* __restrict__ Dl) {
-  const int64_t j = blockIdx.y;
-  for (int64_t a = (int64_t)blockIdx.x * 256 + threadIdx.x; a < ldp; a += (int64_t)gridDim.x * 256) {
-    if (a < d) What[j * ld + a] = W[j * ld + a];
-    Dh[delta_index(j, a, gridDim.y)] = 0;
-    Dl[delta_index(j, a, gridDim.y)] = 0;
-  }
 }
 
 // Dh/Dl = hi/lo of What[j][a] - W[j][a], a < ldp, zero padded, in the staged order of delta_index.
@@ -406,7 +398,7 @@ __device__ __forceinline__ void walk_body(char* smem, int tile, const float* __r
                                           const unsigned short* __restrict__ Htl, int64_t d_out, int64_t d,
                                           int64_t ld, int64_t ldp, int G, int n_rt, int blk, int next_blk,
                                           unsigned char* __restrict__ Q, unsigned short* __restrict__ Dh,
-                                          unsigned short* __restrict__ Dl, float* __restrict__ E) {
+                                          unsigned short* __restrict__ Dl, float* __restrict__ E, bool from_w) {
   float (*tw)[kRows + 1] = reinterpret_cast<float (*)[kRows + 1]>(smem + kWalkTw);      // the targets
   float (*cur)[kRows + 1] = reinterpret_cast<float (*)[kRows + 1]>(smem + kWalkCur);    // the block of What, old values then new ones
   float (*coef)[kBlk] = reinterpret_cast<float (*)[kBlk]>(smem + kWalkCoef);            // coef[a][b] = Ht[i0 + b][i0 + a]
@@ -451,7 +443,8 @@ __device__ __forceinline__ void walk_body(char* smem, int tile, const float* __r
     const int64_t jr = r < n_rows ? j0 + r : j_last;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     wreg[u] = vec_in ? *reinterpret_cast<const f32x4*>(W + jr * ld + i0 + vc) : zero;
-    creg[u] = vec_in ? *reinterpret_cast<const f32x4*>(What + jr * ld + i0 + vc) : zero;
+    // (sequential rounding starts from the weights themselves, whatever What holds)
+    creg[u] = from_w ? wreg[u] : vec_in ? *reinterpret_cast<const f32x4*>(What + jr * ld + i0 + vc) : zero;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (i0 + vc + e >= d) {
@@ -686,13 +679,13 @@ __global__ __launch_bounds__(256) void cd_block_kernel(int n_walk, const float* 
                                                        unsigned char* __restrict__ Q,
                                                        unsigned short* __restrict__ Dh,
                                                        unsigned short* __restrict__ Dl, float* __restrict__ Cout,
-                                                       int gemm_delay, int k_stages) {
+                                                       int gemm_delay, int k_stages, bool from_w) {
   __shared__ __attribute__((aligned(1024))) char smem[kSmemBytes];
   if ((int)blockIdx.x < n_walk) {
     // (the same dealing for the walk: the tiles of a group, which share its coefficients, on as few XCDs as possible)
     const int tile = n_walk % 8 == 0 ? ((int)blockIdx.x % 8) * (n_walk / 8) + (int)blockIdx.x / 8 : (int)blockIdx.x;
     walk_body<LV>(smem, tile, Cin, n_in, W, What, codebook, n_levels, Cd, Hth, Htl, d_out, d, ld, ldp, G,
-                  n_rt, blk, walk_next, Q, Dh, Dl, Cout + (int64_t)n_parts * n_walk * kBlk * kRows);
+                  n_rt, blk, walk_next, Q, Dh, Dl, Cout + (int64_t)n_parts * n_walk * kBlk * kRows, from_w);
   } else {
     // The walk begins with a burst of loads (some 300 KiB per workgroup) and then hardly touches memory;
     // where the GEMM is the shorter of the two, it starts `gemm_delay` ticks of the 100 MHz clock late and
@@ -790,17 +783,14 @@ hipError_t run_assign(bool ldlq, const float* W, float* What, const float* codeb
   const unsigned t64 = (unsigned)(L.ldp / 64);
   // (prep_done: an earlier call with the same H and this workspace has left the split coefficients in place)
   if (ldlq)
-    ldlq_prep_kernel<<<dim3(t64, t64, (unsigned)G), dim3(256), 0, st>>>(H, d_in, L.ldp, Hth, Htl, Cd);
+    ldlq_prep_kernel<<<dim3((unsigned)(4 * tri_count(L.n_blk)), 1, (unsigned)G), dim3(256), 0, st>>>(H, d_in, L.ldp, Hth, Htl, Cd);
   else if (!prep_done)
     cd_prep_kernel<<<dim3(t64 * (t64 + 1) / 2, 1, (unsigned)G), dim3(256), 0, st>>>(H, d_in, L.ldp, Hth, Htl, Cd);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  {
+  if (!ldlq) {                                              // (a sequential pass reads no delta that its walks have not written)
     int64_t bx = (L.ldp + 255) / 256;
     if (bx > 64) bx = 64;
-    if (ldlq)
-      ldlq_init_kernel<<<dim3((unsigned)bx, (unsigned)d_out), dim3(256), 0, st>>>(W, What, d_in, ld, L.ldp, Dh, Dl);
-    else
-      cd_delta_kernel<<<dim3((unsigned)bx, (unsigned)d_out), dim3(256), 0, st>>>(W, What, d_in, ld, L.ldp, Dh, Dl);
+    cd_delta_kernel<<<dim3((unsigned)bx, (unsigned)d_out), dim3(256), 0, st>>>(W, What, d_in, ld, L.ldp, Dh, Dl);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   float* Cbuf[2] = {C, (float*)((char*)C + L.c_bytes)};
@@ -812,7 +802,7 @@ hipError_t run_assign(bool ldlq, const float* W, float* What, const float* codeb
                                                                    n_levels, Cd, Hth, Htl, d_out, d_in, ld, L.ldp, G,   \
                                                                    L.n_rt, L.n_gt, BLK, WNEXT, NEXT, EXCL, Q, Dh, Dl,   \
                                                                    COUT, (NWALK) > 0 ? gemm_delay : 0,                  \
-                                                                   ldlq ? kBlkStages * (NEXT) : (int)(L.ldp / kGemmK))
+                                                                   ldlq ? kBlkStages * (NEXT) : (int)(L.ldp / kGemmK), ldlq)
 #define GQ_LAUNCH_ANY(GRID, NWALK, CIN, NIN, BLK, WNEXT, NEXT, EXCL, COUT)                                              \
   do {                                                                                                                  \
     if (n_levels <= 4) GQ_LAUNCH_BLOCK(4, GRID, NWALK, CIN, NIN, BLK, WNEXT, NEXT, EXCL, COUT);                         \
