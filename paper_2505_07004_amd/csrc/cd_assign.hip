@@ -436,6 +436,7 @@ __device__ __forceinline__ void walk_body(char* smem, int tile, const float* __r
   // vector that starts inside the matrix ends inside the row; coordinates past the end count as zero.
   const int vc = 4 * (lane % 32);                           // first coordinate of this lane's vectors
   const bool vec_in = i0 + vc < d;
+  const float* before = from_w ? W : What;                  // sequential rounding starts from the weights themselves
   f32x4 wreg[8], creg[8];                                   // W stays in registers for the write-back
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
@@ -443,8 +444,7 @@ __device__ __forceinline__ void walk_body(char* smem, int tile, const float* __r
     const int64_t jr = r < n_rows ? j0 + r : j_last;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     wreg[u] = vec_in ? *reinterpret_cast<const f32x4*>(W + jr * ld + i0 + vc) : zero;
-    // (sequential rounding starts from the weights themselves, whatever What holds)
-    creg[u] = from_w ? wreg[u] : vec_in ? *reinterpret_cast<const f32x4*>(What + jr * ld + i0 + vc) : zero;
+    creg[u] = vec_in ? *reinterpret_cast<const f32x4*>(before + jr * ld + i0 + vc) : zero;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (i0 + vc + e >= d) {
