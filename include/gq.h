@@ -272,7 +272,8 @@ size_t gq_objective_workspace_bytes(int64_t d_out, int64_t d_in, int32_t G);
  *   H        [G, d_in, d_in]  device fp32; only the upper triangle (incl. diagonal)
  *                             of each H[k] is read (symmetry supplies the rest)
  *   obj      [G]              device fp64
- *   obj_row  [d_out]          device fp32, or NULL if not wanted
+ *   obj_row  [d_out]          device fp32, or NULL if not wanted (obj is then summed another,
+ *                             cheaper way: equal up to rounding, below 1e-5 relative)
  *   workspace  at least gq_objective_workspace_bytes() bytes, 256-byte aligned
  *
  * Errors: GQ_ERR_NULLPTR, GQ_ERR_SHAPE (d_out <= 0, d_in <= 0, G <= 0,
